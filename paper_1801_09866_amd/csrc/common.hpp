@@ -278,7 +278,7 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 a) {
 // value where lo is subnormal. Exponents are held in [14, 254], so that the
 // scale and its inverse are normal; 255 (a non-finite value) has no packed form.
 __device__ __forceinline__ float split_scale(int e) { return __uint_as_float((unsigned)(267 - e) << 23); }
-__device__ __forceinline__ float split_unscale(int e) { return __uint_as_float((unsigned)(e - 13) << 23); }
+__device__ __forceinline__ int split_unscale(int e) { return e - 140; }   // exponent of the inverse
 __device__ __forceinline__ int split_exp(unsigned max_bits) {
     const int e = (int)(max_bits >> 23);
     return e < 14 ? 14 : e;

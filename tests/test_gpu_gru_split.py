@@ -188,3 +188,21 @@ def test_bf16_packed_rows(E, H, L, M, qmode, digits):
         err = (g.double() - want).abs()
         assert bool((err <= bound).all()), (l, float((err / bound).max()))
         x = g.bfloat16().double()
+
+
+def parts_scaled(es, hs, wis, whs, E=128, H=256, M=40):
+    m, w = make(E, H, 1)
+    w["emb"] *= es
+    w["W_ih"][0] *= wis
+    w["W_hh"][0] *= whs
+    vec, w1 = rows(M, m)
+    return m, w, vec * hs, w1
+
+
+@pytest.mark.parametrize("s,k", [(1e-36, 1.0), (1e30, 1.0), (1e-34, 40.0)])
+def test_weights_and_rows_far_apart(s, k):
+    """Operands near either end of fp32's range whose sums are not (k: their size)."""
+    m, w, vec, w1 = parts_scaled(s, s, k / s, k / s)
+    got, _ = run(m, w, vec, w1)
+    want, bound = step64(m, w, vec, w1)
+    assert bool(((got.double() - want).abs() <= bound).all())
