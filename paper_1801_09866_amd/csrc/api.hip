@@ -196,10 +196,11 @@ size_t layout(const rnnlm_config &c, char *base, rn::Dev &d, void **packed) {
         }
     }
     d.ln_part = cv.take<float2>((size_t)256 * rn::lognorm_tiles(c.V));
-    d.w_max = cv.take<unsigned>(2);
+    d.w_bad = cv.take<unsigned>(2);
     for (int l = 0; l < 2; ++l) {   // packed operand rows, addressed by 32-bit offsets
         const int Kx = l == 0 ? c.E : c.H;
         const bool sp = c.wdtype == RNNLM_F32;
+        d.w_exp[l] = cv.take<uint2>(split_operands(c) && l < c.L ? c.H : 0);
         const size_t xl = sp ? rn::part_lines<true>(Kx) : rn::part_lines<false>(Kx);
         const size_t hl = sp ? rn::part_lines<true>(c.H) : rn::part_lines<false>(c.H);
         const size_t row = packed_operands(c) && l < c.L ? (xl + hl) * 128 : 0;

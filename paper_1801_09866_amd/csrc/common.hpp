@@ -108,7 +108,9 @@ struct Dev {
     // GRU operand value, times a power of two, as the sum of two fp16 numbers. Packed weights (Wp), and per layer
     // one packed row [Kx + H] per history of each session (apk, rows of
     // apk_row bytes, session-major; null: the rows would not fit 32-bit offsets and
-    // the GRU takes its plain path). w_max: bits of each layer's largest |weight|.
+    // the GRU takes its plain path). w_exp: per layer and unit, the exponents of
+    // its weight rows' scales (bytes: reset, update, candidate; x: input part, y:
+    // recurrent part). w_bad: 1 where a layer has a non-finite weight.
     // bf16 models pack rows too for launches that compute on them (split is
     // set per launch): bf16 values, 64 per line; each part of a row ends at a pair of
     // lines (apk_h: where its history part begins).
@@ -117,7 +119,9 @@ struct Dev {
     unsigned apk_row[2], apk_h[2];
     int sess0;   // session whose state the pointers below address
     int split;
-    unsigned *w_max;
+    uint2 *w_exp[2];
+    const uint2 *wel;   // w_exp of the layer a GRU launch computes
+    unsigned *w_bad;
     const void *Wih[2], *Whh[2];   // the caller's weights
     const void *Wf[2];             // packed weights in the order the matrix instructions read them
     // history cache: index + dense entries
@@ -271,8 +275,8 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 a) {
     return r;
 }
 
-// Split operands. A row (or a layer's weights) whose largest |value| has the
-// biased exponent e is scaled by 2^(140 - e), which puts that value into
+// Split operands. A row (of operands, or of one gate and unit's weights) whose
+// largest |value| has the biased exponent e is scaled by 2^(140 - e), which puts that value into
 // [2^13, 2^14), and each scaled value v becomes hi = fp16(v), lo = fp16(v - hi).
 // hi + lo is v within 2^-22 of itself, and within 2^-39 of the row's largest
 // value where lo is subnormal. Exponents are held in [14, 254], so that the

@@ -206,3 +206,21 @@ def test_weights_and_rows_far_apart(s, k):
     got, _ = run(m, w, vec, w1)
     want, bound = step64(m, w, vec, w1)
     assert bool(((got.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("gate", [0, 1, 2])
+@pytest.mark.parametrize("where", ["W_ih", "W_hh", "W_ih1", "W_hh1"])
+@pytest.mark.parametrize("value", [30.0, 1e4, 1e6, 1e8])
+def test_one_large_weight(where, value, gate):
+    """It costs the units that do not use it nothing."""
+    m, w = make(128, 256, 2)
+    vec, w1 = rows(40, m)
+    l = int(where.endswith("1"))
+    w[where[:4]][l][gate * m.H + 9, 11] = value
+    got, _ = run(m, w, vec, w1)
+    want, bound = step64(m, w, vec, w1)
+    err = (got.double() - want).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+    others = torch.ones(m.L * m.H, dtype=torch.bool, device="cuda")
+    others[l * m.H + 9] = False
+    assert float(err[:, others].norm() / want[:, others].norm()) < 3e-7
