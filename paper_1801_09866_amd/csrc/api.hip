@@ -196,7 +196,7 @@ size_t layout(const rnnlm_config &c, char *base, rn::Dev &d, void **packed) {
         }
     }
     d.ln_part = cv.take<float2>((size_t)256 * rn::lognorm_tiles(c.V));
-    d.w_bad = cv.take<unsigned>(2);
+    d.w_flags = cv.take<unsigned>(2);
     for (int l = 0; l < 2; ++l) {   // packed operand rows, addressed by 32-bit offsets
         const int Kx = l == 0 ? c.E : c.H;
         const bool sp = c.wdtype == RNNLM_F32;
@@ -231,7 +231,7 @@ size_t layout(const rnnlm_config &c, char *base, rn::Dev &d, void **packed) {
     d.f_roww = cv.take<int>(mh);
     d.f_rowh = cv.take<unsigned long long>(mh);
     d.f_rowdst = cv.take<unsigned long long>(mh);
-    d.f_rowi = cv.take<int>(mh);
+    d.f_rowi = cv.take<unsigned long long>(mh);
     d.f_hval = cv.take<float>(mh * LH);
     const bool bf = c.wdtype == RNNLM_BF16;
     d.f_hbf = cv.take<uint16_t>(bf ? mh * LH : 8);

@@ -20,7 +20,7 @@ constexpr int kPlanMaxQuery = 8192;
 enum Ctr {
     C_HC_SIZE = 0, C_SC_SIZE, C_FRAMES, C_QUERIES, C_SCORE_HITS, C_QUERY_DUPS, C_COMPUTED,
     C_HISTS, C_HIST_HITS, C_HIST_DUPS, C_GRU_ROWS, C_HIST_INS, C_HIST_REJ, C_SCORE_INS,
-    C_SCORE_REJ, C_FRAME_M, C_STAGED, C_NEAR_CAP, C_DONE, C_FRAME_SLOW, C_N
+    C_SCORE_REJ, C_FRAME_M, C_STAGED, C_NEAR_CAP, C_DONE, C_ROW_FLAGS, C_FRAME_FLAGS, C_N
 };
 
 // QRec flag bits above the 2-bit base status (COMPUTED or Q_DUP)
@@ -72,10 +72,16 @@ struct QRec {
 // one 16-byte record.
 struct HistRec {
     u64 hash;   // 64-bit key hash
-    int slot;   // history-cache slot found before the frame; if none, negative: ~slot holds the
-                // exponents of the row's packed copies (0 without split operands)
+    int slot;   // history-cache slot found before the frame; if none, negative: ~slot is the
+                // row's ScaleCode (0 without split operands)
     int w1;     // GRU input word (clamped into [0, V))
 };
+
+// What a GRU launch on split operands has to know of its weights (w_flags) and
+// rows (C_ROW_FLAGS, gathered by the keys kernel; C_FRAME_FLAGS, set by the
+// planner): some have no packed form; some have parts with scales of their own
+// (bit F_SCALE0 << layer).
+enum GruFlags : unsigned { F_PLAIN = 1, F_SCALE0 = 2 };
 
 // Cache probes read the linear-probe sequence kProbeWin records at a time,
 // one record per lane (tables have at least 64 slots).
@@ -110,7 +116,7 @@ struct Dev {
     // apk_row bytes, session-major; null: the rows would not fit 32-bit offsets and
     // the GRU takes its plain path). w_exp: per layer and unit, the exponents of
     // its weight rows' scales (bytes: reset, update, candidate; x: input part, y:
-    // recurrent part). w_bad: 1 where a layer has a non-finite weight.
+    // recurrent part). w_flags: per layer, GruFlags of its weights.
     // bf16 models pack rows too for launches that compute on them (split is
     // set per launch): bf16 values, 64 per line; each part of a row ends at a pair of
     // lines (apk_h: where its history part begins).
@@ -121,7 +127,7 @@ struct Dev {
     int split;
     uint2 *w_exp[2];
     const uint2 *wel;   // w_exp of the layer a GRU launch computes
-    unsigned *w_bad;
+    unsigned *w_flags;
     const void *Wih[2], *Whh[2];   // the caller's weights
     const void *Wf[2];             // packed weights in the order the matrix instructions read them
     // history cache: index + dense entries
@@ -144,7 +150,7 @@ struct Dev {
     int *f_roww;      // GRU input word (w-1) of row r
     u64 *f_rowh;      // address of row r's history vector (all layers)
     u64 *f_rowdst;    // where row r writes its h'
-    int *f_rowi;      // split operands: row r's history index | exponents of its packed rows << 16, << 24
+    u64 *f_rowi;      // packed operands: row r's history index | its ScaleCode << 32
     float *f_hval;    // [max_hist][LH] h' of rows the cache did not admit
     // bf16 weights: the GEMM's A operand, rounded to bf16 once per frame
     uint16_t *f_hbf;  // [max_hist][LH] each history row (written by the keys kernel)
@@ -275,8 +281,9 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 a) {
     return r;
 }
 
-// Split operands. A row (of operands, or of one gate and unit's weights) whose
-// largest |value| has the biased exponent e is scaled by 2^(140 - e), which puts that value into
+// Split operands. A row (the input or the recurrent part of a GRU row's operands,
+// or of one gate and unit's weights) whose largest |value| has the
+// biased exponent e is scaled by 2^(140 - e), which puts that value into
 // [2^13, 2^14), and each scaled value v becomes hi = fp16(v), lo = fp16(v - hi).
 // hi + lo is v within 2^-22 of itself, and within 2^-39 of the row's largest
 // value where lo is subnormal. Exponents are held in [14, 254], so that the
@@ -286,6 +293,30 @@ __device__ __forceinline__ int split_unscale(int e) { return e - 140; }   // exp
 __device__ __forceinline__ int split_exp(unsigned max_bits) {
     const int e = (int)(max_bits >> 23);
     return e < 14 ? 14 : e;
+}
+
+// Exponents of the two parts, from the bits of their largest |value|s. A part
+// takes the other's where that is larger by at most 2^8 (its values then
+// are within 2^-31 of its largest), or where it is all zeros: equal exponents
+// spare the GRU a change of scale between the parts, and the parts of
+// ordinary rows and weights are that close.
+struct PartExp {
+    int x, h;
+};
+__device__ __forceinline__ PartExp part_exps(unsigned mx, unsigned mh) {
+    const int x = split_exp(mx), h = split_exp(mh), e = max(x, h);
+    return {mx == 0 || x + 8 >= e ? e : x, mh == 0 || h + 8 >= e ? e : h};
+}
+
+// ScaleCode: the exponents of a history's packed rows in 31 bits. The second
+// layer's input (the first layer's h') is scaled by its bound, which is at least 1.
+constexpr unsigned kNoScale = 0x7FFFFFFFu;   // no packed form
+__device__ __forceinline__ unsigned scale_code(PartExp e0, PartExp e1) {
+    return (unsigned)e0.x | ((unsigned)e0.h << 8) | ((unsigned)e1.h << 16) | ((unsigned)(e1.x - 127) << 24);
+}
+__device__ __forceinline__ PartExp scale_of(unsigned code, int layer) {
+    if (layer == 0) return {(int)(code & 0xFF), (int)((code >> 8) & 0xFF)};
+    return {(int)((code >> 24) & 0x7F) + 127, (int)((code >> 16) & 0xFF)};
 }
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ void split8(const float (&v)[8], float scale, uint4 &hi, uint4 &lo) {

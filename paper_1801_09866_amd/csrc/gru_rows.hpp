@@ -18,6 +18,7 @@ struct RowSrc {
 struct Rows {
     int n;
     int moff[kMaxSessions + 1];
+    int sess[kMaxSessions];   // relative to the launch's Dev
     long long sofs[kMaxSessions];
 };
 
@@ -48,7 +49,10 @@ __device__ __forceinline__ Rows make_rows(const Dev &d, const SessList &sl, cons
     Rows R;
     R.n = sl.n;
 #pragma unroll
-    for (int e = 0; e < kMaxSessions; ++e) R.sofs[e] = (long long)sl.sess[e < sl.n ? e : 0] * d.sess_stride;
+    for (int e = 0; e < kMaxSessions; ++e) {
+        R.sess[e] = sl.sess[e < sl.n ? e : 0];
+        R.sofs[e] = (long long)R.sess[e] * d.sess_stride;
+    }
     R.moff[0] = 0;
 #pragma unroll
     for (int e = 0; e < kMaxSessions; ++e)
@@ -111,11 +115,11 @@ __device__ __forceinline__ T *row_ptr(const Rows &R, T *arr, int m, size_t strid
 
 // session of row m of the whole launch (absolute), for the packed rows, which
 // lie outside the sessions' strided state
-__device__ __forceinline__ int row_session(const Dev &d, const SessList &sl, const Rows &R, int m) {
-    int s = sl.sess[0];
+__device__ __forceinline__ int row_session(const Dev &d, const Rows &R, int m) {
+    int s = R.sess[0];
 #pragma unroll
     for (int e = 1; e < kMaxSessions; ++e)
-        if (e < R.n && m >= R.moff[e]) s = sl.sess[e];
+        if (e < R.n && m >= R.moff[e]) s = R.sess[e];
     return d.sess0 + s;
 }
 

@@ -254,7 +254,6 @@ __global__ __launch_bounds__(PT) void k_frame_plan(Dev d0, LaunchBlock<MULTI> fb
     __shared__ long long c[C_N];             // the counters, read once and written back once
     __shared__ int s_cnt[2];
     __shared__ int s_htot, s_qtot;
-    __shared__ int s_slow;             // some GRU row has no packed form
     __shared__ int s_more[3];          // race rounds: some key lost in round k (k mod 3)
     __shared__ uint32_t s_ovf[2 * OVF];  // keys still racing after the last table: histories, then queries
 
@@ -304,7 +303,7 @@ __global__ __launch_bounds__(PT) void k_frame_plan(Dev d0, LaunchBlock<MULTI> fb
     for (int k = tid; k < tab_slots / 4; k += PT)   // slot counts are multiples of 64
         reinterpret_cast<uint4 *>(tab)[k] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
     if (tid < 2) s_cnt[tid] = 0;
-    if (tid == 0) s_more[0] = s_slow = 0;
+    if (tid == 0) s_more[0] = 0;
     // the loads have landed: keep what other threads read
 #pragma unroll
     for (int r = 0; r < HR; ++r) {
@@ -582,9 +581,7 @@ __global__ __launch_bounds__(PT) void k_frame_plan(Dev d0, LaunchBlock<MULTI> fb
                 d.f_roww[row] = h_w1[r];
                 d.f_rowh[row] = (u64)src;
                 d.f_rowdst[row] = (u64)hp;
-                const int ex = ~h_slot[r] & 0xFFFF;   // 0 without split operands
-                d.f_rowi[row] = i | (ex << 16);
-                if ((ex & 0xFF) == 0xFF || (ex >> 8) == 0xFF) s_slow = 1;
+                d.f_rowi[row] = (u64)(unsigned)~h_slot[r] << 32 | (unsigned)i;
                 if (d.wdtype == RNNLM_BF16) d.f_rowhb[row] = (u64)(d.f_hbf + (size_t)i * d.LH);
             }
             if (f.h_status) f.h_status[i] = (uint8_t)st;
@@ -620,7 +617,8 @@ __global__ __launch_bounds__(PT) void k_frame_plan(Dev d0, LaunchBlock<MULTI> fb
         const long long room = d.cap_hist > hc_size ? d.cap_hist - hc_size : 0;
         const int ins = (int)(M < room ? M : room);
         c[C_FRAME_M] = M;
-        c[C_FRAME_SLOW] = s_slow;
+        c[C_FRAME_FLAGS] = c[C_ROW_FLAGS];
+        c[C_ROW_FLAGS] = 0;   // for the next frame's keys kernel
         c[C_HC_SIZE] = hc_size + ins;
         c[C_FRAMES] += 1;
         c[C_HISTS] += n;

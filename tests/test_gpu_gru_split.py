@@ -38,11 +38,18 @@ def step64(m, w, vec, w1):
         gi, gh = x @ Wi.t() + b, h @ Wh.t()
         K = Wi.shape[1] + H
         unit = 3 * 2.0 ** -22 + (3 * K / 32 + 10) * 2.0 ** -24
-        # the row's scale follows its largest value: what is far below it is
-        # off by up to 2^-39 of that
-        floor = 2.0 ** -38 * torch.maximum(x.abs().amax(1), h.abs().amax(1))[:, None]
-        ei = unit * (x.abs() @ Wi.abs().t() + b.abs()) + dx @ Wi.abs().t() + floor * Wi.abs().sum(1)
-        eh = unit * (h.abs() @ Wh.abs().t()) + floor * Wh.abs().sum(1)
+        # a part's scale follows its own largest value, or the other part's
+        # where that is at most 2^8 times as large: what is far below it is off
+        # by up to 2^-39 of that. A second layer's input is scaled by its bound.
+        own = lambda a, other: 2.0 ** -38 * torch.minimum(torch.maximum(a, other), 256 * a)
+        ax, ah = x.abs().amax(1), h.abs().amax(1)
+        if l:
+            ax = vec[:, :H].double().abs().amax(1).clamp(min=1.0)
+        fx, fh = own(ax, ah)[:, None], own(ah, ax)[:, None]
+        wi, wh = Wi.abs().amax(1), Wh.abs().amax(1)
+        ei = (unit * (x.abs() @ Wi.abs().t() + b.abs()) + dx @ Wi.abs().t() + fx * Wi.abs().sum(1)
+              + own(wi, wh) * x.abs().sum(1)[:, None])
+        eh = unit * (h.abs() @ Wh.abs().t()) + fh * Wh.abs().sum(1) + own(wh, wi) * h.abs().sum(1)[:, None]
         r, z = torch.sigmoid(gi[:, :H] + gh[:, :H]), torch.sigmoid(gi[:, H:2 * H] + gh[:, H:2 * H])
         n = torch.tanh(gi[:, 2 * H:] + r * gh[:, 2 * H:])
         dr, dz = (ei + eh)[:, :H] / 4, (ei + eh)[:, H:2 * H] / 4
@@ -224,3 +231,20 @@ def test_one_large_weight(where, value, gate):
     others = torch.ones(m.L * m.H, dtype=torch.bool, device="cuda")
     others[l * m.H + 9] = False
     assert float(err[:, others].norm() / want[:, others].norm()) < 3e-7
+
+
+@pytest.mark.parametrize("es,hs,wis,whs", [(1e-6, 1.0, 1e6, 1.0), (1.0, 1e-6, 1.0, 1e6), (1e-20, 1.0, 1e20, 1.0), (1.0, 1e-20, 1.0, 1e20),
+                                           (1e-3, 1.0, 1e3, 1.0), (1.0, 1e-36, 1.0, 1e36), (1e-36, 1.0, 1e36, 1.0), (1.0, 0.0, 1.0, 1.0),
+                                           (1.0, 1.0, 1.0, 0.0), (1.0, 1.0, 0.0, 1.0), (0.0, 1.0, 1.0, 1.0), (1.0, 1.0, 1.0, 1e-30),
+                                           (1.0, 1e-30, 1.0, 1e-10), (1e-30, 1.0, 1e-10, 1.0)])
+@pytest.mark.parametrize("E,H,M", [(64, 64, 5), (128, 256, 40), (512, 1024, 150), (512, 1024, 600)])
+def test_input_and_recurrent_parts_of_other_sizes(es, hs, wis, whs, E, H, M):
+    """One part's values small, its weights large: its products count as much
+    as the other part's, so each part keeps its own precision."""
+    m, w, vec, w1 = parts_scaled(es, hs, wis, whs, E, H, M)
+    got, _ = run(m, w, vec, w1)
+    want, bound = step64(m, w, vec, w1)
+    err = (got.double() - want).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+    # what fp32 sums show
+    assert float(err.norm() / want.norm()) < 3e-7
