@@ -121,11 +121,29 @@ uint32_t pow2_at_least(long long n) {
 
 int sessions_of(const rnnlm_config &c) { return c.sessions > 0 ? c.sessions : 1; }
 
-// The GRU runs on packed operands unless the history keys are exact: exact keys
+// 128-byte lines of a packed row of layer l: input part, recurrent part
+struct RowLines {
+    size_t x, h;
+};
+RowLines row_lines(const rnnlm_config &c, int l) {
+    const int Kx = l == 0 ? c.E : c.H;
+    if (c.wdtype == RNNLM_F32) return {(size_t)rn::part_lines<true>(Kx), (size_t)rn::part_lines<true>(c.H)};
+    return {(size_t)rn::part_lines<false>(Kx), (size_t)rn::part_lines<false>(c.H)};
+}
+size_t packed_row_bytes(const rnnlm_config &c, int l) {
+    const RowLines n = row_lines(c, l);
+    return (n.x + n.h) * 128 * c.max_hist * sessions_of(c);
+}
+
+// The GRU runs on packed operands unless the history keys are exact (exact keys
 // hold every bit of h', so a decode loop's keys follow the other kernel's
-// summation order. fp32 models always do; bf16 models do in launches of at most
-// kPackedRows histories.
-bool packed_operands(const rnnlm_config &c) { return c.qmode != RNNLM_Q_EXACT; }
+// summation order) or the packed rows lie beyond 32-bit offsets. fp32 models
+// always do; bf16 models do in launches of at most kPackedRows histories.
+bool packed_operands(const rnnlm_config &c) {
+    bool fit = true;
+    for (int l = 0; l < c.L; ++l) fit = fit && packed_row_bytes(c, l) < (1ull << 32);
+    return c.qmode != RNNLM_Q_EXACT && fit;
+}
 bool split_operands(const rnnlm_config &c) { return packed_operands(c) && c.wdtype == RNNLM_F32; }
 
 int code_words(const rnnlm_config &c) {
@@ -198,18 +216,17 @@ size_t layout(const rnnlm_config &c, char *base, rn::Dev &d, void **packed) {
     d.ln_part = cv.take<float2>((size_t)256 * rn::lognorm_tiles(c.V));
     d.w_flags = cv.take<unsigned>(2);
     for (int l = 0; l < 2; ++l) {   // packed operand rows, addressed by 32-bit offsets
-        const int Kx = l == 0 ? c.E : c.H;
-        const bool sp = c.wdtype == RNNLM_F32;
-        d.w_exp[l] = cv.take<uint2>(split_operands(c) && l < c.L ? c.H : 0);
-        const size_t xl = sp ? rn::part_lines<true>(Kx) : rn::part_lines<false>(Kx);
-        const size_t hl = sp ? rn::part_lines<true>(c.H) : rn::part_lines<false>(c.H);
-        const size_t row = packed_operands(c) && l < c.L ? (xl + hl) * 128 : 0;
-        d.apk_h[l] = (unsigned)(xl * 128);
+        d.apk[l] = nullptr;
+        d.w_exp[l] = nullptr;
+        d.Wf[l] = packed[l];
+        if (!packed_operands(c) || l >= c.L) continue;
+        const RowLines n = row_lines(c, l);
+        if (split_operands(c)) d.w_exp[l] = cv.take<uint2>(c.H);
         // fp32: in place of the row-major weights; bf16: beside them
-        d.Wf[l] = row && !sp ? cv.take<char>((xl + hl) * (c.H / 16) * 6144) : packed[l];
-        const size_t bytes = row * c.max_hist * sessions_of(c);
-        d.apk_row[l] = (unsigned)row;
-        d.apk[l] = row && bytes < (1ull << 32) ? cv.take<char>(bytes) : nullptr;
+        else d.Wf[l] = cv.take<char>((n.x + n.h) * (c.H / 16) * 6144);
+        d.apk_h[l] = (unsigned)(n.x * 128);
+        d.apk_row[l] = (unsigned)((n.x + n.h) * 128);
+        d.apk[l] = cv.take<char>(packed_row_bytes(c, l));
     }
     // one session's state; sessions 1.. repeat it sess_stride bytes apart
     const size_t mh = c.max_hist, mq = c.max_query > 0 ? c.max_query : 1;
@@ -308,7 +325,7 @@ RNNLM_API int rnnlm_create(const rnnlm_config *cfg, const rnnlm_weights *w, void
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     for (int l = 0; l < cfg->L; ++l) {
         rn::launch_pack_layer(d, l, w->W_ih[l], w->W_hh[l], packed[l], s);
-        if (!packed_operands(*cfg) || cfg->wdtype != RNNLM_BF16 || !d.apk[l]) continue;
+        if (!packed_operands(*cfg) || cfg->wdtype != RNNLM_BF16) continue;
         rn::launch_pack_split(d, l, s);
         // the zeros that fill up odd parts; the keys kernel writes the rest of a row
         rn::launch_fill_u32(d.apk[l], 0u, (long long)d.apk_row[l] / 4 * cfg->max_hist * sessions_of(*cfg), s);
@@ -379,7 +396,7 @@ RNNLM_API int rnnlm_score_frames(rnnlm_t *ctx, const rnnlm_frame *frames, const 
     const int s0 = fb.sess[0];   // the launches see the context from entry 0's session
     rn::Dev d = rn::session_view(ctx->dev, s0);
     if (c.wdtype == RNNLM_BF16)
-        d.split = packed_operands(c) && maxh <= rn::kPackedRows && d.apk[0] && (c.L == 1 || d.apk[1]);
+        d.split = packed_operands(c) && maxh <= rn::kPackedRows;
     int sess_abs[rn::kMaxSessions];
     for (int e = 0; e < fb.n; ++e) {
         sess_abs[e] = fb.sess[e];

@@ -113,8 +113,7 @@ struct Dev {
     // Split operands (split: fp32 weights, sign or rounded history keys): every
     // GRU operand value, times a power of two, as the sum of two fp16 numbers. Packed weights (Wp), and per layer
     // one packed row [Kx + H] per history of each session (apk, rows of
-    // apk_row bytes, session-major; null: the rows would not fit 32-bit offsets and
-    // the GRU takes its plain path). w_exp: per layer and unit, the exponents of
+    // apk_row bytes, session-major; null: none of this applies). w_exp: per layer and unit, the exponents of
     // its weight rows' scales (bytes: reset, update, candidate; x: input part, y:
     // recurrent part). w_flags: per layer, GruFlags of its weights.
     // bf16 models pack rows too for launches that compute on them (split is

@@ -248,3 +248,26 @@ def test_input_and_recurrent_parts_of_other_sizes(es, hs, wis, whs, E, H, M):
     assert bool((err <= bound).all()), float((err / bound).max())
     # what fp32 sums show
     assert float(err.norm() / want.norm()) < 3e-7
+
+
+def test_packed_rows_beyond_32_bit_offsets():
+    """Eight sessions of 2048 histories of 65,600 operands: more packed rows
+    than 32-bit offsets reach. Such a model keeps the kernel of exact keys, and
+    its results to the bit."""
+    m, w = make(65536, 64, 1, V=20)
+    vec, w1 = rows(70, m)
+    out = {}
+    for qmode in (R.Q_SIGN, R.Q_EXACT):
+        sc = R.Scorer(m, w, qmode, 0, max_hist=2048, max_query=1, cap_hist=256, cap_query=16, sessions=8)
+        words = torch.zeros((70, 3), dtype=torch.int32, device="cuda")
+        words[:, 0] = w1.int()
+        e = torch.zeros(0, dtype=torch.int32, device="cuda")
+        out[qmode] = sc.score_frame(vec, words, e, e)["hnew"].clone()
+        torch.cuda.synchronize()
+        assert sc.stats()["gru_rows"] == 70
+    assert torch.equal(out[R.Q_SIGN], out[R.Q_EXACT])
+    want, bound = step64(m, w, vec, w1)
+    err = (out[R.Q_SIGN].double() - want).abs()
+    # this kernel's sums: one rounding per four products
+    bound = bound + (65600 / 4) * 2.0 ** -24 * (1 + want.abs())
+    assert bool((err <= bound).all())
