@@ -115,7 +115,7 @@ struct Dev {
     // one packed row [Kx + H] per history of each session (apk, rows of
     // apk_row bytes, session-major; null: none of this applies). w_exp: per layer and unit, the exponents of
     // its weight rows' scales (bytes: reset, update, candidate; x: input part, y:
-    // recurrent part). w_flags: per layer, GruFlags of its weights.
+    // recurrent part), and in x's last byte 1 for a unit with a non-finite weight. w_flags: per layer, GruFlags of its weights.
     // bf16 models pack rows too for launches that compute on them (split is
     // set per launch): bf16 values, 64 per line; each part of a row ends at a pair of
     // lines (apk_h: where its history part begins).

@@ -271,3 +271,34 @@ def test_packed_rows_beyond_32_bit_offsets():
     # this kernel's sums: one rounding per four products
     bound = bound + (65600 / 4) * 2.0 ** -24 * (1 + want.abs())
     assert bool((err <= bound).all())
+
+
+@pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("rows_each", [45, 300])
+def test_non_finite_embedding_leaves_the_other_rows(L, rows_each):
+    """One session meets a word with a non-finite embedding: no other row of
+    either session changes by a bit."""
+    m, w = make(64, 192, L)
+    vec, w1 = rows(2 * rows_each, m)
+    w1[w1 == 7] = 8
+    w1[3] = 7
+    base, _ = run(m, w, vec, w1, sessions=2)
+    w["emb"][7, 5] = float("inf")
+    got, _ = run(m, w, vec, w1, sessions=2)
+    keep = torch.arange(2 * rows_each, device="cuda") != 3
+    assert torch.equal(got[keep], base[keep])
+    assert not torch.equal(got[3], base[3])
+
+
+@pytest.mark.parametrize("where", ["W_ih", "W_hh", "W_hh1"])
+@pytest.mark.parametrize("gate", [0, 1, 2])
+@pytest.mark.parametrize("M", [5, 150])
+def test_non_finite_weight_leaves_the_other_units(where, gate, M):
+    m, w = make(64, 192, 2 if where == "W_hh1" else 1)
+    vec, w1 = rows(M, m)
+    base, _ = run(m, w, vec, w1)
+    l = int(where.endswith("1"))
+    w[where[:4]][l][gate * m.H + 9, 11] = float("inf")
+    got, _ = run(m, w, vec, w1)
+    keep = torch.arange(m.L * m.H, device="cuda") != l * m.H + 9
+    assert torch.equal(got[:, keep], base[:, keep])
