@@ -48,10 +48,15 @@ def test_scales(us, hs, n):
 
 @pytest.mark.parametrize("n", [3, 256])
 def test_one_tile_out_of_range(n):
-    """Only the tile that meets the value recomputes; the others are unchanged."""
+    """Only the tile that meets the value recomputes; the others are unchanged:
+    without that tile's words, the result is the same to the bit."""
     U, b, h = data(1000, 128, n)
+    masked = b.clone()
+    masked[416:624] = -1e30   # the words of tile 2
+    base = R.log_normalizer_static(U, masked, h).clone()
     U[500, 7] = 100.0
     check(U, b, h)
+    assert torch.equal(R.log_normalizer_static(U, masked, h), base)
 
 
 @pytest.mark.parametrize("n", [3, 256])
@@ -72,3 +77,23 @@ def test_non_finite(n):
     b2[300] = float("-inf")
     want = torch.logsumexp(h.double() @ U[keep].double().t() + b[keep].double(), dim=1)
     assert float((R.log_normalizer_static(U, b2, h).double() - want).abs().max()) < 3e-6
+
+
+@pytest.mark.parametrize("n", [3, 100, 256])
+def test_row_0_counts_for_its_own_tile_only(n):
+    """Word 0 (sentence start) out of range: the other tiles are unchanged. And
+    a tile of tiny values beside an ordinary word 0 keeps its precision."""
+    U, b, h = data(1000, 128, n)
+    masked = b.clone()
+    masked[:208] = -1e30   # the words of tile 0
+    base = R.log_normalizer_static(U, masked, h).clone()
+    U[0, 7] = 100.0
+    assert torch.equal(R.log_normalizer_static(U, masked, h), base)
+    U, b, h = data(209, 128, n)
+    b[:208] = -1e30
+    b[208] = 0.0
+    U[208] *= 1e-7   # the only word that counts: the result is its logit
+    got = R.log_normalizer_static(U, b, h).double()
+    want = h.double() @ U[208].double()
+    S = h.double().abs() @ U[208].double().abs()
+    assert bool(((got - want).abs() <= S * (3 * 2.0 ** -22 + (3 * 128 / 32 + 4) * 2.0 ** -24)).all())
