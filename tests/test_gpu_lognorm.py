@@ -97,3 +97,43 @@ def test_row_0_counts_for_its_own_tile_only(n):
     want = h.double() @ U[208].double()
     S = h.double().abs() @ U[208].double().abs()
     assert bool(((got - want).abs() <= S * (3 * 2.0 ** -22 + (3 * 128 / 32 + 4) * 2.0 ** -24)).all())
+
+
+@pytest.mark.parametrize("big", [5.0, 1e4, 1e30])
+@pytest.mark.parametrize("n", [3, 64, 65, 100, 200, 256])
+def test_one_row_out_of_range(n, big):
+    """A history beyond the split's fixed range has a scale of its own, beside
+    ordinary and tiny ones."""
+    U, b, h = data(1000, 128, n)
+    h[n // 2] *= big
+    h[n // 2 - 1] *= 1e-9
+    check(U, b, h)
+
+
+@pytest.mark.parametrize("n", [3, 100, 256])
+def test_unequal_words_of_a_tile(n):
+    """Words far above and far below the fixed range in one tile, rows alike."""
+    U, b, h = data(1000, 128, n)
+    U *= torch.logspace(-20, 3, 1000, device="cuda")[torch.randperm(1000, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))][:, None]
+    h *= torch.logspace(-6, 1, n, device="cuda")[:, None]
+    check(U, b, h)
+
+
+@pytest.mark.parametrize("n", [3, 64, 100, 256])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf")])
+def test_infinite_row(n, value):
+    """A row with an infinity: -inf where it takes every logit there, else NaN
+    (two logits of +inf, or infinities of both signs), as in fp32; the other
+    rows are right."""
+    U, b, h = data(1000, 128, n)
+    base = R.log_normalizer_static(U, b, h).clone()
+    i = n // 2
+    h[i, 70] = value
+    got = R.log_normalizer_static(U, b, h).clone()
+    assert bool(torch.isnan(got[i]))
+    others = torch.arange(n, device="cuda") != i
+    assert float((got - base)[others].abs().max()) < 3e-6
+    U[:, 70] = -U[:, 70].abs() * (1 if value > 0 else -1)   # every logit of the row is -inf
+    assert float(R.log_normalizer_static(U, b, h)[i]) == float("-inf")
+    U[:, 70] = -U[:, 70]                                     # every logit is +inf
+    assert bool(torch.isnan(R.log_normalizer_static(U, b, h)[i]))
