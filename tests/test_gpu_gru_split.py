@@ -6,7 +6,8 @@ bound per value follows the arithmetic: an operand's two parts miss it by at
 most 2^-22 of itself and lo x lo (2^-22) is left out, so a product is within
 3 x 2^-22, and the fp32 sums of 3 K / 32 matrix instructions and four partial
 sums round by at most 2^-24 of S = sum |w| |a| each. Non-finite weights and
-embeddings have no split form; they must give fp32's infinities and NaNs."""
+embeddings have no split form; they must give fp32's infinities and NaNs, and
+change nothing else."""
 import numpy as np
 import pytest
 import torch
@@ -62,9 +63,9 @@ def step64(m, w, vec, w1):
     return torch.cat(out, 1), torch.cat(bnd, 1)
 
 
-def run(m, w, vec, w1, qmode=R.Q_SIGN, sessions=1):
+def run(m, w, vec, w1, qmode=R.Q_SIGN, sessions=1, digits=0):
     B = vec.shape[0] // sessions
-    sc = R.Scorer(m, w, qmode, 0, max_hist=B, max_query=1, cap_hist=2048, cap_query=16, sessions=sessions)
+    sc = R.Scorer(m, w, qmode, digits, max_hist=B, max_query=1, cap_hist=2048, cap_query=16, sessions=sessions)
     words = torch.zeros((vec.shape[0], 3), dtype=torch.int32, device="cuda")
     words[:, 0] = w1.int()
     e = torch.zeros(0, dtype=torch.int32, device="cuda")
@@ -302,3 +303,18 @@ def test_non_finite_weight_leaves_the_other_units(where, gate, M):
     got, _ = run(m, w, vec, w1)
     keep = torch.arange(m.L * m.H, device="cuda") != l * m.H + 9
     assert torch.equal(got[:, keep], base[:, keep])
+
+
+@pytest.mark.parametrize("qmode,digits", [(R.Q_SIGN, 0), (R.Q_SIGDIG, 2)])
+@pytest.mark.parametrize("E,H,L", [(576, 128, 1), (1088, 64, 2), (4160, 64, 1), (128, 1024, 2)])
+@pytest.mark.parametrize("M", [1, 17, 129, 300])
+def test_key_modes_and_long_embeddings(E, H, L, M, qmode, digits):
+    """Rows packed by a wave and by a block; embeddings longer than what either reads before its cache probe."""
+    m, w = make(E, H, L)
+    vec, w1 = rows(M, m)
+    got, st = run(m, w, vec, w1, qmode=qmode, digits=digits)
+    assert st["gru_rows"] == M
+    want, bound = step64(m, w, vec, w1)
+    err = (got.double() - want).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+    assert float(err.norm() / want.norm()) < 3e-7

@@ -1,11 +1,14 @@
 """Every GRU path at the Large model's shapes, against the oracle.
 
 A warm Large run has few new history keys per frame (Sec. 3: the history
-cache absorbs the rest), so most frames run the narrow path (at most 32
-rows) and the others the tiled path, whose row tiles shrink with the row
-count. fp32 tiles are 16 hidden units wide, and 64 wide once the 16-unit
-tiles would need more than one per CU (above 512 rows at H = 1024); bf16
-tiles are 16 wide up to 256 rows, 32 wide up to 1024 and 64 wide above.
+cache absorbs the rest), and a cold one many; the row count of a launch picks
+the tile. Under exact keys: at most 32 rows the narrow path, above it tiles
+16 hidden units wide, and 64 wide once the 16-unit tiles would need more than
+one per CU (fp32, above 512 rows at H = 1024; bf16 tiles are 16 wide up to 256
+rows, 32 up to 1024 and 64 above). Under sign keys fp32 launches, and bf16
+launches of at most 1024 histories, run on packed operands: tiles 16 units
+wide up to 128 rows, 32 above, of one to four row blocks; other bf16 launches
+run as under exact keys.
 Here each path runs at E = 512, H = 1024: one fp32 layer (K = 1536), and two
 bf16 layers (K = 1536, then 2048). A first frame puts some keys in the
 history cache; the frame under test then has exactly M new history keys,
@@ -20,7 +23,7 @@ import pytest
 import torch
 
 from harness import ATOL, BF16_ATOL, RTOL, close, log
-from oracle import HC_HIT, H_DUP, Q_SCORE_HIT, Q_SIGN, Oracle
+from oracle import HC_HIT, H_DUP, Q_EXACT, Q_SCORE_HIT, Q_SIGN, Oracle
 from paper_1801_09866_amd import rnnlm as R
 from paper_1801_09866_amd.workload import BF16, F32, ModelCfg
 
@@ -32,14 +35,17 @@ MODELS = {
     "bf16": ModelCfg(V=V, E=512, H=1024, L=2, wdtype=BF16, maxent_log2=16, maxent_order=4),
 }
 ROWS = (1, 15, 16, 17, 32, 33, 100, 256, 257)
-ROWS_WIDE = {"fp32": (513, 1100), "bf16": (1025, 1600)}   # 64-unit tiles
+ROWS_WIDE = {"fp32": (513, 1100), "bf16": (1025, 1600)}   # 64-unit tiles under exact keys
 N_WARM = 24      # keys of the first frame
 N_CACHED = 8     # first-frame histories repeated in the frame under test
 KEYS = ("h_hash", "h_status", "h_rep", "q_status", "q_rep")
 
 
-def path_of(name, M, one):
-    if M <= 16 and one:
+def path_of(name, M, sessions, qm):
+    hists = M + len(range(0, M, 5)) + N_CACHED * sessions
+    if qm == Q_SIGN and (name == "fp32" or hists <= 1024):
+        return "packed32" if M > 128 else "packed16"
+    if M <= 16 and sessions == 1:
         return "narrow_preloaded"
     if M <= 32:
         return "narrow"
@@ -50,11 +56,12 @@ def path_of(name, M, one):
 
 def cases():
     for name in MODELS:
-        for M in ROWS + ROWS_WIDE[name]:
-            for sessions in (1, 2):
-                # two sessions split the rows: session 0 has M - M // 3, session 1 has M // 3
-                yield pytest.param(name, M, sessions,
-                                   id="%s-%s-M%d-s%d" % (name, path_of(name, M, sessions == 1), M, sessions))
+        for qm in (Q_SIGN, Q_EXACT):
+            for M in ROWS + ROWS_WIDE[name]:
+                for sessions in (1, 2):
+                    # two sessions split the rows: session 0 has M - M // 3, session 1 has M // 3
+                    yield pytest.param(name, M, sessions, qm, id="%s-%s-%s-M%d-s%d" % (
+                        name, "sign" if qm == Q_SIGN else "exact", path_of(name, M, sessions, qm), M, sessions))
 
 
 _W = {}
@@ -129,15 +136,15 @@ def compare(out, res, fr, bf16, tag):
     assert ok, "%s: scores differ by %.3g" % (tag, err)
 
 
-@pytest.mark.parametrize("name,M,sessions", list(cases()))
-def test_gru_path_at_large_dims(name, M, sessions):
+@pytest.mark.parametrize("name,M,sessions,qm", list(cases()))
+def test_gru_path_at_large_dims(name, M, sessions, qm):
     m = MODELS[name]
     w = weights(name)
     rng = np.random.default_rng(M * 7 + sessions)
     split = [M] if sessions == 1 else [M - M // 3, M // 3]
     kw = dict(max_hist=2048, max_query=4096, cap_hist=1 << 12, cap_query=1 << 14)
-    g = R.Scorer(m, w, Q_SIGN, 0, sessions=sessions, **kw)
-    orc = [Oracle(m.V, m.E, m.H, m.L, m.maxent_log2, m.maxent_order, w, Q_SIGN, 0,
+    g = R.Scorer(m, w, qm, 0, sessions=sessions, **kw)
+    orc = [Oracle(m.V, m.E, m.H, m.L, m.maxent_log2, m.maxent_order, w, qm, 0,
                   cap_hist=kw["cap_hist"], cap_query=kw["cap_query"], seed=R.DEFAULT_SEED)
            for _ in range(sessions)]
     warm = [warm_frame(rng, m) for _ in range(sessions)]
@@ -152,7 +159,7 @@ def test_gru_path_at_large_dims(name, M, sessions):
         assert res.gru_rows == N_WARM
         compare(outs[k], res, warm[k], m.wdtype == BF16, "%s warm s%d" % (name, k))
     frames = [frame_under_test(rng, m, warm[k], split[k]) for k in range(sessions)]
-    log("  %s M=%d sessions=%d: frame under test, path %s" % (name, M, sessions, path_of(name, M, sessions == 1)))
+    log("  %s M=%d sessions=%d: frame under test, path %s" % (name, M, sessions, path_of(name, M, sessions, qm)))
     if sessions == 1:
         outs = [g.score_frame(*to_dev(frames[0]))]
     else:

@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from harness import ATOL, BF16_ATOL, RTOL, close, log
-from oracle import Q_SIGDIG, Q_SIGN, Oracle
+from oracle import Q_EXACT, Q_SIGDIG, Q_SIGN, Oracle
 from paper_1801_09866_amd import rnnlm as R
 from paper_1801_09866_amd.workload import BF16, F32, ModelCfg
 
@@ -42,11 +42,14 @@ def frame(rng, pool, n_h, n_q):
 
 
 @pytest.mark.parametrize("sizes,caps,qm", [
-    ((6, 9, 12), (1 << 12, 1 << 14), (Q_SIGN, 0)),        # rows of all sessions <= 32: narrow path
-    ((40, 25, 60), (1 << 12, 1 << 14), (Q_SIGN, 0)),      # medium path
-    ((150, 120, 200), (1 << 12, 1 << 14), (Q_SIGN, 0)),   # 64 x 32 tiles
+    ((6, 9, 12), (1 << 12, 1 << 14), (Q_SIGN, 0)),        # packed operands: one row block
+    ((40, 25, 60), (1 << 12, 1 << 14), (Q_SIGN, 0)),      # row blocks shared by sessions
+    ((150, 120, 200), (1 << 12, 1 << 14), (Q_SIGN, 0)),   # many row blocks
     ((30, 20, 50), (40, 90), (Q_SIGN, 0)),                # small caches: in-order admission per session
     ((33, 7, 52), (1 << 12, 1 << 14), (Q_SIGDIG, 2)),     # one key block per history
+    ((6, 9, 12), (1 << 12, 1 << 14), (Q_EXACT, 0)),       # exact keys: narrow path (at most 32 rows)
+    ((150, 120, 200), (1 << 12, 1 << 14), (Q_EXACT, 0)),  # exact keys: 16-unit tiles
+    ((30, 20, 50), (40, 90), (Q_EXACT, 0)),
 ])
 def test_sessions_match_independent_contexts_and_the_oracle(sizes, caps, qm):
     rng = np.random.default_rng(sum(sizes))
@@ -116,18 +119,19 @@ def test_a_device_error_in_one_session_is_sticky_for_the_context():
     assert g.stats()["device_error"] == 0
 
 
+@pytest.mark.parametrize("qm", [Q_SIGN, Q_EXACT], ids=["sign", "exact"])
 @pytest.mark.parametrize("wd", [F32, BF16], ids=["fp32", "bf16"])
-def test_eight_sessions_of_maximal_frames(wd):
+def test_eight_sessions_of_maximal_frames(wd, qm):
     """The largest launch the API allows: 8 sessions, each frame at the
     planner's maxima (2048 histories, 8192 queries), with uniform targets and
     a second block that repeats half of each session's histories and many of
     its queries (cache hits). Every session must equal a context of its own,
-    and one session the oracle. At H = 128 the 8-session launches run the
-    64-unit tiles (fp32: both blocks, 16384 and 8192 GRU rows; bf16: the
-    first block) and the 32-unit bf16 tiles (the second block), while a
-    context of its own runs the 16-unit tiles on at most 2048 rows; bf16
-    results are compared at the bf16 tolerance, since the tiles' summation
-    orders differ."""
+    and one session the oracle. fp32 sign keys: packed tiles of four row blocks,
+    looping over the launch. Otherwise, at H = 128, the 8-session launches run
+    the 64-unit tiles (fp32: both blocks, 16384 and 8192 GRU rows; bf16: the
+    first block) and the 32-unit bf16 tiles (the second block), while a context
+    of its own runs the 16-unit tiles on at most 2048 rows; bf16 results are
+    compared at the bf16 tolerance, since the tiles' summation orders differ."""
     m = ModelCfg(V=M.V, E=M.E, H=M.H, L=M.L, wdtype=wd, maxent_log2=M.maxent_log2, maxent_order=M.maxent_order)
     tol = (BF16_ATOL, 0.0) if wd == BF16 else (ATOL, RTOL)
     rng = np.random.default_rng(88)
@@ -135,8 +139,8 @@ def test_eight_sessions_of_maximal_frames(wd):
     S, n_h, n_q = 8, 2048, 8192
     caps = (1 << 14, 1 << 16)
     kw = dict(max_hist=n_h, max_query=n_q, cap_hist=caps[0], cap_query=caps[1])
-    multi = R.Scorer(m, w, Q_SIGN, 0, sessions=S, **kw)
-    solo = R.Scorer(m, w, Q_SIGN, 0, **kw)
+    multi = R.Scorer(m, w, qm, 0, sessions=S, **kw)
+    solo = R.Scorer(m, w, qm, 0, **kw)
     d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     blocks = []
     for t in range(2):
@@ -169,7 +173,7 @@ def test_eight_sessions_of_maximal_frames(wd):
             if t == 1:
                 assert (outs[k]["q_status"] == R.Q_SCORE_HIT).sum().item() > n_q // 4, k
     assert multi.stats()["device_error"] == 0
-    o = Oracle(m.V, m.E, m.H, m.L, m.maxent_log2, m.maxent_order, w, Q_SIGN, 0,
+    o = Oracle(m.V, m.E, m.H, m.L, m.maxent_log2, m.maxent_order, w, qm, 0,
                cap_hist=caps[0], cap_query=caps[1], seed=R.DEFAULT_SEED)
     o.score_frame(*blocks[0][3])
     res = o.score_frame(*blocks[1][3])
