@@ -136,9 +136,10 @@ size_t packed_row_bytes(const rnnlm_config &c, int l) {
 }
 
 // The GRU runs on packed operands unless the history keys are exact (exact keys
-// hold every bit of h', so a decode loop's keys follow the other kernel's
-// summation order) or the packed rows lie beyond 32-bit offsets. fp32 models
-// always do; bf16 models do in launches of at most kPackedRows histories.
+// hold every bit of h', and of a decode loop that feeds h' back; with the other
+// kernel its outputs stay what they were to the bit) or the packed rows lie
+// beyond 32-bit offsets. fp32 models always do; bf16 models do in launches of at
+// most kPackedRows histories.
 bool packed_operands(const rnnlm_config &c) {
     bool fit = true;
     for (int l = 0; l < c.L; ++l) fit = fit && packed_row_bytes(c, l) < (1ull << 32);

@@ -10,10 +10,11 @@
 //   r = sigmoid(a_r), z = sigmoid(a_z), n = tanh(a_nx + b_n + r * a_nh),
 //   h' = (1 - z) * n + z * h.
 // The epilogue is fused: no gate pre-activation ever reaches HBM.
-// This kernel serves exact history keys, and bf16 models in launches of more than
-// kPackedRows histories. Exact keys hold every bit of a history vector, so
-// the keys of a decode loop that feeds h' back depend on the order of these sums;
-// the other launches take the packed operands of gru_tiles.hip.
+// This kernel serves exact history keys, bf16 models in launches of more than
+// kPackedRows histories, and models whose packed rows would not fit 32-bit
+// offsets; the other launches take the packed operands of gru_tiles.hip. Exact
+// keys hold every bit of a history vector, so they stay with these sums (whose
+// order follows the launch's row count, through the choice of tile).
 #include <type_traits>
 
 #include "gru_rows.hpp"
