@@ -115,6 +115,13 @@ def gru_peak(m, qm):
     return PEAK["bf16_mfma_TFs"] if m.wdtype == 1 else PEAK["fp32_mfma_TFs" if qm == 0 else "split_mfma_TFs"]
 
 
+def gru_products(m, qm):
+    """What the GRU's products are made of (the line's dtype names operands and sums)."""
+    if m.wdtype == 1:
+        return "bf16 MFMA"
+    return "fp32 MFMA" if qm == 0 else "f32 as hi + lo fp16: three fp16 MFMAs, f32 sums"
+
+
 def algorithmic_work(cfg, st, qm, frames):
     """Algorithmic FLOPs / bytes of each stage over a span with stats `st`.
 
@@ -318,7 +325,8 @@ def main():
         "config": {"workload": "%s_%s: V=%d E=%d H=%d L=%d MaxEnt 2^%d orders 2..%d, %d queries/frame"
                                % (cfg.name, qmode_name(qm, qk), m.V, m.E, m.H, m.L, m.maxent_log2,
                                   m.maxent_order, cfg.queries),
-                   "frames_timed": K, "queries_timed": queries, "qmode": qmode_name(qm, qk)},
+                   "frames_timed": K, "queries_timed": queries, "qmode": qmode_name(qm, qk),
+                   "gru_products": gru_products(m, qm)},
         "frames_per_s": round(K / secs, 1),
         "computed_queries_per_s": round(span["computed"] / secs, 1),
         "gru_rows_per_s": round(span["gru_rows"] / secs, 1),
@@ -671,7 +679,8 @@ def main_check(args, cfg):
         "config": {"workload": "check: V=%d E=%d H=%d L=%d, %d histories/frame, EXACT keys, logsumexp over V%s"
                                % (m.V, m.E, m.H, m.L, cfg.hists,
                                   " of NCE + MaxEnt (orders 2..%d) logits" % m.maxent_order if args.maxent else ""),
-                   "frames_timed": K, "maxent": bool(args.maxent)},
+                   "frames_timed": K, "maxent": bool(args.maxent), "gru_products": gru_products(m, qm),
+                   "lognorm_products": "f32 as hi + lo fp16: three fp16 MFMAs, f32 sums"},
         "wall_ms": round(wall * 1e3, 3),
         # NCE self-normalisation: how far log Z is from 0 over the timed histories
         "logz": {"mean": round(float(z.mean()), 6), "sd": round(float(z.std()), 6),
@@ -771,7 +780,8 @@ def main_sessions(args, cfg):
         "scaling": "weak", "vs_baseline": None, "dtype": "f32" if m.wdtype == 0 else "bf16-weights/f32-accumulate",
         "data": "synthetic",
         "config": {"workload": "%s_%s split into %d independent sessions of %d frames, one frame of each per launch"
-                               % (cfg.name, qmode_name(qm, qk), S, F), "sessions": S, "qmode": qmode_name(qm, qk)},
+                               % (cfg.name, qmode_name(qm, qk), S, F), "sessions": S, "qmode": qmode_name(qm, qk),
+                   "gru_products": gru_products(m, qm)},
         "frames_per_s": round(span["frames"] / secs, 1),
         "computed_queries_per_s": round(span["computed"] / secs, 1),
         "score_hit_ratio": hit(span["score_hits"], span["queries"]),

@@ -23,6 +23,16 @@
  * a 4 MiB static device array per GPU, the scratch of the allocation-free
  * rnnlm_log_normalizer_static.
  *
+ * Precision: with fp32 weights every sum is kept in fp32. Under EXACT keys the
+ * GRU multiplies fp32 operands. Under SIGN and SIGDIG keys, and in the
+ * normalisers, operands are split into two fp16 numbers with a power-of-two
+ * scale per row (one history, embedding or output vector; one gate and unit's
+ * input or recurrent weights): an operand is held within 2^-22 of itself or, if
+ * smaller, 2^-30 of the largest of its row (the second layer's input: 2^-30 of
+ * the larger of 1 and the largest of the first layer's history), and a product
+ * within 3 x 2^-22. Results of ordinary models are as close to the exact value
+ * as with fp32 products. Infinities and NaNs give what fp32 gives.
+ *
  * Streams: `stream` arguments are hipStream_t values passed as void* (NULL =
  * the default stream). All work is enqueued on that stream and nothing blocks
  * the host, except rnnlm_create (which synchronises once) and rnnlm_get_stats.

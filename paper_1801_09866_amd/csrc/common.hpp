@@ -285,7 +285,7 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 a) {
 // or of one gate and unit's weights) whose largest |value| has the
 // biased exponent e is scaled by 2^(140 - e), which puts that value into
 // [2^13, 2^14), and each scaled value v becomes hi = fp16(v), lo = fp16(v - hi).
-// hi + lo is v within 2^-22 of itself, and within 2^-39 of the row's largest
+// hi + lo is v within 2^-22 of itself, and within 2^-38 of the row's largest
 // value where lo is subnormal. Exponents are held in [14, 254], so that the
 // scale and its inverse are normal; 255 (a non-finite value) has no packed form.
 __device__ __forceinline__ float split_scale(int e) { return __uint_as_float((unsigned)(267 - e) << 23); }
@@ -297,7 +297,7 @@ __device__ __forceinline__ int split_exp(unsigned max_bits) {
 
 // Exponents of the two parts, from the bits of their largest |value|s. A part
 // takes the other's where that is larger by at most 2^8 (its values then
-// are within 2^-31 of its largest), or where it is all zeros: equal exponents
+// are within 2^-30 of its largest), or where it is all zeros: equal exponents
 // spare the GRU a change of scale between the parts, and the parts of
 // ordinary rows and weights are that close.
 struct PartExp {

@@ -264,8 +264,8 @@ def span(a):
         print("%-24s %8d %10.2f " % (fam, len(per[fam]["ns"]), mean(per[fam]["ns"]) / 1e3)
               + " ".join("%16.1f" % mean(per[fam][c]) if per[fam].get(c) else "%16s" % "-" for c in cols))
     print("# per frame, rn::k_gru or rn::k_gru_split (bytes: counter units times the calibration scales)")
-    print("%6s %10s %14s %14s %10s %12s %12s" % ("frame", "us", "MfmaFlopsF32", "MfmaFlopsBF16", "MfmaUtil",
-                                                  "fetch_MB", "write_MB"))
+    print("%6s %10s %14s %14s %14s %10s %12s %12s" % ("frame", "us", "MfmaFlopsF32", "MfmaFlopsBF16", "MfmaFlopsF16",
+                                                       "MfmaUtil", "fetch_MB", "write_MB"))
     for i in range(lo, hi):
         def val(key, c):
             if key not in runs:
@@ -275,9 +275,9 @@ def span(a):
                 xs = [v.get(c, 0.0) for fam, v in fr[i - lo] if fam.startswith("rn::k_gru")]
                 per_leg.append(sum(xs) if c != "MfmaUtil" else mean(xs))
             return mean(per_leg)
-        print("%6d %10.2f %14.0f %14.0f %10.1f %12.2f %12.2f" % (
+        print("%6d %10.2f %14.0f %14.0f %14.0f %10.1f %12.2f %12.2f" % (
             i, val("ns", "ns") / 1e3, val("mfma", "MfmaFlopsF32"), val("mfma", "MfmaFlopsBF16"),
-            val("mfma", "MfmaUtil"), val("fetch", "FETCH_SIZE") * scale["FETCH_SIZE"] / 1e6,
+            val("mfma", "MfmaFlopsF16"), val("mfma", "MfmaUtil"), val("fetch", "FETCH_SIZE") * scale["FETCH_SIZE"] / 1e6,
             val("write", "WRITE_SIZE") * scale["WRITE_SIZE"] / 1e6))
     if a.fetch and a.write:
         for fam in sorted(per):

@@ -41,7 +41,7 @@ def step64(m, w, vec, w1):
         unit = 3 * 2.0 ** -22 + (3 * K / 32 + 10) * 2.0 ** -24
         # a part's scale follows its own largest value, or the other part's
         # where that is at most 2^8 times as large: what is far below it is off
-        # by up to 2^-39 of that. A second layer's input is scaled by its bound.
+        # by up to 2^-38 of that. A second layer's input is scaled by its bound.
         own = lambda a, other: 2.0 ** -38 * torch.minimum(torch.maximum(a, other), 256 * a)
         ax, ah = x.abs().amax(1), h.abs().amax(1)
         if l:
