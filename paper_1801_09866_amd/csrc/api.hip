@@ -139,7 +139,7 @@ size_t packed_row_bytes(const rnnlm_config &c, int l) {
 // hold every bit of h', and of a decode loop that feeds h' back; with the other
 // kernel its outputs stay what they were to the bit) or the packed rows lie
 // beyond 32-bit offsets. fp32 models always do; bf16 models do in launches of at
-// most kPackedRows histories.
+// most packed_hists histories.
 bool packed_operands(const rnnlm_config &c) {
     bool fit = true;
     for (int l = 0; l < c.L; ++l) fit = fit && packed_row_bytes(c, l) < (1ull << 32);
@@ -397,7 +397,7 @@ RNNLM_API int rnnlm_score_frames(rnnlm_t *ctx, const rnnlm_frame *frames, const 
     const int s0 = fb.sess[0];   // the launches see the context from entry 0's session
     rn::Dev d = rn::session_view(ctx->dev, s0);
     if (c.wdtype == RNNLM_BF16)
-        d.split = packed_operands(c) && maxh <= rn::kPackedRows;
+        d.split = packed_operands(c) && maxh <= rn::packed_hists(c.H);
     int sess_abs[rn::kMaxSessions];
     for (int e = 0; e < fb.n; ++e) {
         sess_abs[e] = fb.sess[e];

@@ -339,13 +339,15 @@ __host__ __device__ __forceinline__ int part_lines(int K) {
 
 // A launch of at most this many histories runs a bf16 GRU on packed rows. The
 // host knows the histories only, which bound the rows (the uncached ones). The
-// packed tiles are faster while their four-way split of K keeps about one tile
-// per CU busy; the other kernel's 64-unit tiles read each operand less often.
-// GRU us on other and packed tiles, one layer of E = 512, H = 1024, by rows: 64:
-// 12.7 and 7.9, 512: 20.1 and 16.0, 768: 25.0 and 23.3, 1024: 26.9 and 27.0,
-// 1536: 36.8 and 37.5, 2048: 43.1 and 48.2; two layers, 1024: 55.4 and 57.1. At
-// H = 512 they cross at 1400 rows, at H = 256 at 2048.
-constexpr int kPackedRows = 1024;
+// packed tiles are faster while their four-way split of K keeps a few tiles
+// per CU busy; the other kernel's 64-unit tiles read each operand less often, and
+// wide models have more tiles. GRU us on other and packed tiles, one layer, by
+// rows. E = 512, H = 1024: 64: 12.7 and 7.9, 512: 20.1 and 16.0, 768: 25.0 and
+// 23.3, 1024: 26.9 and 27.0, 2048: 43.1 and 48.2 (two layers, 1024: 55.4 and
+// 57.1; E = 64, 1024: 23.4 and 25.4). E = 512, H = 2048: 256: 26.6 and 20.2, 512:
+// 34.9 and 34.1, 768: 46.4 and 47.5, 1024: 53.2 and 61.7. At H = 512 they cross at
+// 1400 rows, at H = 256 at 2048.
+__host__ __forceinline__ int packed_hists(int H) { return H <= 1024 ? 1024 : (1 << 20) / H; }
 
 // A history handle is bad when null or not 16-byte aligned.
 __device__ __forceinline__ bool bad_handle(u64 p) { return p == 0 || (p & 15); }

@@ -11,7 +11,7 @@
 //   h' = (1 - z) * n + z * h.
 // The epilogue is fused: no gate pre-activation ever reaches HBM.
 // This kernel serves exact history keys, bf16 models in launches of more than
-// kPackedRows histories, and models whose packed rows would not fit 32-bit
+// packed_hists histories, and models whose packed rows would not fit 32-bit
 // offsets; the other launches take the packed operands of gru_tiles.hip. Exact
 // keys hold every bit of a history vector, so they stay with these sums (whose
 // order follows the launch's row count, through the choice of tile).

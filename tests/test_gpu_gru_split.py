@@ -160,10 +160,12 @@ def test_non_finite_operands(where, value):
 
 
 @pytest.mark.parametrize("qmode,digits", [(R.Q_SIGN, 0), (R.Q_SIGDIG, 2)])
-@pytest.mark.parametrize("E,H,L", [(64, 64, 1), (192, 64, 2), (64, 320, 2), (576, 128, 1), (512, 1024, 2), (4160, 64, 1)])
-@pytest.mark.parametrize("M", [1, 16, 17, 64, 65, 129, 513, 1024])
+@pytest.mark.parametrize("E,H,L", [(64, 64, 1), (192, 64, 2), (64, 320, 2), (576, 128, 1), (512, 1024, 2), (4160, 64, 1),
+                                   (64, 2048, 1)])
+@pytest.mark.parametrize("M", [1, 16, 17, 64, 65, 129, 512, 513, 1024])
 def test_bf16_packed_rows(E, H, L, M, qmode, digits):
-    """bf16 models in launches of at most 1024 histories: odd and even numbers
+    """bf16 models in launches of at most 1024 histories (512 at H = 2048, where
+    more take the other kernel): odd and even numbers
     of 64-value lines in either part, rows longer than a thread group reads at
     once. Each layer against float64 on the bf16 operands it really had (the
     second layer's input is the first one's h', rounded), so the bound is that
